@@ -1,0 +1,364 @@
+"""Performance cases of the library: what a user of the verify / draft steps has it do, from the smallest call to
+the largest batch.
+
+Kinds of a case
+  verify   one target step over N branches x T rows, logits and accept / resample (`VerifyContext.step`), with an
+           optional candidate tree, ragged private contexts and narrow weights
+  draft    one autoregressive token of every branch (`VerifyContext.draft_step`)
+  prefill  a prompt taken into the shared cache, then the first decode step on it (`VerifyContext.prefill_shared`)
+  accept   the stateless accept / resample on distributions made elsewhere (`accept_resample`)
+  sched    the rounds-scheduled execution end to end (`sched_run`)
+
+Model shapes are the repository's: the 7B and 13B decoders it verifies with and the two-layer draft model.  There are
+no checkpoints here, so weights are random with the traits of a trained decoder that the path depends on: matrices
+N(0, 0.02^2), the two projections that write the residual stream scaled by 1 / sqrt(2 layers), so that the stream keeps
+the token it came from, and an LM head that maps every token to a successor with a confidence that varies by token.
+Next-token distributions are then peaked as a trained model's are, drafts that follow the same successors are mostly
+accepted, and what is sampled does not hang on the last digits of 32000 nearly equal probabilities.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2406_18200_amd import ModelShape, VerifyContext, accept_resample
+from paper_2406_18200_amd.binding import sched_run, tree_sizes
+
+DEVICE = "cuda:0"
+VOCAB = 32000
+#          layers, d_model, heads, head_dim, d_ff
+MODELS = {"7b": (32, 4096, 32, 128, 11008), "13b": (40, 5120, 40, 128, 13824), "draft": (2, 768, 12, 64, 3072)}
+GAP = 15.0        # logit distance of a token's successor from the bulk, on average over tokens
+FP4_MIDS = (0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0)   # between the E2M1 magnitudes 0, 0.5, 1, 1.5, 2, 3, 4, 6
+
+
+# ------------------------------------------------------------------------------------------------- the cases
+def _verify(model, N, gamma, S, R, temperature, dtype="bf16", ragged=False, tree="", greedy=False):
+    return dict(kind="verify", model=model, dtype=dtype, N=N, gamma=gamma, S=S, R=R, ragged=ragged, tree=tree,
+                greedy=greedy, temperature=temperature)
+
+
+def listed():
+    return [
+        # the two smallest calls: one draft token for eight thoughts (launch- and latency-bound), and a host that
+        # brings its own logits and only needs the accept / resample rule
+        dict(kind="draft", model="draft", dtype="bf16", N=8, S=256, R=20, temperature=1.0, name="draft_8"),
+        dict(kind="accept", N=16, gamma=6, tree="", logits=True, static=False, temperature=1.0, name="accept_16x6"),
+        # the paper's own setting: three thoughts of four drafts on a 7B target
+        dict(_verify("7b", 3, 4, 512, 0, 0.7), name="verify_7b_3x4"),
+        # the same in four-bit weights
+        dict(_verify("7b", 3, 4, 512, 0, 0.7, dtype="bf16w4"), name="verify_7b_w4_3x4"),
+        # three thoughts with candidate trees: 13 fed rows each (an odd number of rows in all)
+        dict(_verify("7b", 3, 3, 512, 40, 0.7, tree="4,2,1"), name="verify_7b_tree_3x421"),
+        # state evaluation: every branch scores a state of its own, nothing shared, ragged contexts
+        dict(_verify("7b", 8, 4, 0, 1024, 0.7, ragged=True), name="verify_7b_states_8x4"),
+        # a 13B target on a long prompt, in bf16 and in one-byte weights
+        dict(_verify("13b", 8, 5, 4096, 0, 0.7), name="verify_13b_8x5"),
+        dict(_verify("13b", 8, 5, 4096, 0, 0.7, dtype="bf16w8"), name="verify_13b_w8_8x5"),
+        # the wide search of the benchmark, and the largest step there is
+        dict(_verify("7b", 16, 6, 2048, 128, 1.0), name="verify_7b_16x6"),
+        dict(_verify("7b", 128, 6, 2048, 128, 1.0), name="verify_7b_128x6"),
+        # a prompt of odd length taken in through the wide search's context
+        dict(kind="prefill", model="7b", dtype="bf16", N=16, gamma=6, S=1999, name="prefill_7b_1999"),
+        # the whole loop: draft model and target on two streams, drafts verified in rounds
+        dict(kind="sched", model="7b", N=3, gamma=4, S=512, new=32, unit=3, temperature=0.3, name="sched_7b_3x4"),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case of the ranges above: any number of branches and drafts up to the 768 rows of a step, any context
+    length up to what the listed cases hold."""
+    kind = rng.choices(("verify", "draft", "prefill", "accept", "sched"), (10, 3, 2, 2, 1))[0]
+    if kind == "verify":
+        model = rng.choices(("7b", "13b"), (3, 1))[0]
+        tree = rng.choice(("2,2,1", "4,2,1", "3,2")) if rng.random() < 0.15 else ""
+        rows = tree_sizes([int(k) for k in tree.split(",")])[1] if tree else 0
+        gamma = tree.count(",") + 1 if tree else rng.randint(1, 8)
+        rows = rows or gamma
+        dtype = rng.choices(("bf16", "bf16w8", "bf16w4"), (6, 1, 1))[0]
+        # (13B and narrow weights: up to 128 rows, so that no drawn step costs more than the largest listed one)
+        N = max(1, min(_log(rng, 1, 128), (768 if model == "7b" and dtype == "bf16" else 128) // rows))
+        alone = rng.random() < 0.2                                    # nothing shared
+        S = 0 if alone else _log(rng, 48, 4096)
+        R = min(_log(rng, 16, 1024), 16384 // N) if alone or rng.random() < 0.6 else 0
+        return _verify(model, N, gamma, S, R, rng.choice((0.7, 1.0)), dtype=dtype, ragged=R > 0 and rng.random() < 0.5,
+                       tree=tree, greedy=not tree and rng.random() < 0.15)
+    if kind == "draft":
+        return dict(kind=kind, model=rng.choice(("draft", "draft", "7b")), dtype="bf16", N=_log(rng, 1, 64), S=_log(rng, 16, 2048),
+                    R=rng.randint(1, 64), temperature=rng.choice((0.7, 1.0)))
+    if kind == "prefill":
+        N = _log(rng, 2, 128)
+        return dict(kind=kind, model=rng.choice(("7b", "draft")), dtype="bf16", N=N, gamma=6, S=min(_log(rng, 33, 2048), 20 * 6 * N))
+    if kind == "accept":
+        return dict(kind=kind, N=_log(rng, 1, 128), gamma=rng.randint(1, 8), tree="", logits=rng.random() < 0.5,
+                    static=rng.random() < 0.5, temperature=rng.choice((0.7, 1.0)))
+    return dict(kind=kind, model="7b", N=rng.randint(2, 6), gamma=rng.randint(2, 6), S=_log(rng, 64, 1024), new=rng.randint(8, 32),
+                unit=rng.randint(1, 3), temperature=0.3)
+
+
+# ------------------------------------------------------------------------------------------------- inputs
+def _randn(shape, gen, std=1.0, dtype=torch.bfloat16):
+    return torch.randn(shape, generator=gen, device=DEVICE, dtype=dtype).mul_(std)
+
+
+def _narrow(w, dtype):
+    """A float matrix -> (codes, scales) of the narrow formats: e4m3 with a scale per row, MXFP4 with one per 32 inputs."""
+    w = w.float()
+    if dtype == "bf16w8":
+        scale = (w.abs().amax(dim=1) / 448.0).clamp_min(1e-30)
+        return (w / scale[:, None]).clamp(-448.0, 448.0).to(torch.float8_e4m3fn).view(torch.uint8), scale
+    blocks = w.view(w.shape[0], -1, 32)
+    exp = (torch.floor(torch.log2(blocks.abs().amax(dim=2).clamp_min(1e-30))) - 2.0).clamp(-126, 127)
+    mag = (blocks / torch.exp2(exp)[:, :, None]).abs()
+    code = torch.bucketize(mag, torch.tensor(FP4_MIDS, device=DEVICE), out_int32=True).to(torch.uint8)
+    code = (code | ((blocks < 0).to(torch.uint8) << 3)).view(w.shape[0], -1)
+    return (code[:, 0::2] | (code[:, 1::2] << 4)).contiguous(), (exp + 127).to(torch.uint8)
+
+
+def _successors(gen):
+    return torch.randperm(VOCAB, generator=gen, device=DEVICE)
+
+
+def _weights(model, dtype, gen, successor):
+    L, d, H, dh, F = MODELS[model]
+    resid = 0.02 / math.sqrt(2 * L)
+    shapes = {"wq": (H * dh, d, 0.02), "wk": (H * dh, d, 0.02), "wv": (H * dh, d, 0.02), "wo": (d, H * dh, resid),
+              "wgate": (F, d, 0.02), "wup": (F, d, 0.02), "wdown": (d, F, resid)}
+    narrow = dtype in ("bf16w8", "bf16w4")
+    layers = []
+    for _ in range(L):
+        layer = {}
+        for name, (rows, cols, std) in shapes.items():
+            w = _randn((rows, cols), gen, std)
+            if narrow:
+                layer[name], layer["s" + name[1:]] = _narrow(w, dtype)
+            else:
+                layer[name] = w
+        for name in ("norm_attn", "norm_ffn"):
+            layer[name] = _randn((d,), gen, 0.02).add_(1.0)
+        layers.append(layer)
+    emb = _randn((VOCAB, d), gen)
+    # logit of a token's successor: the stream keeps about 0.7 of the (unit variance) embedding through the final norm
+    gap = _randn((VOCAB, 1), gen, 2.0, torch.float32).add_(GAP) / (0.7 * d)
+    head = _randn((VOCAB, d), gen, 0.02, torch.float32).index_add_(0, successor, emb.float() * gap)
+    out = {"layers": layers, "tok_emb": emb, "norm_final": _randn((d,), gen, 0.02).add_(1.0)}
+    if narrow:
+        out["lm_head"], out["lm_head_scale"] = _narrow(head, dtype)
+    else:
+        out["lm_head"] = head.to(torch.bfloat16)
+    return out
+
+
+def _context(model, dtype, gen, successor, N, T, S, R):
+    """A context of the given capacities whose shared cache holds S synthetic tokens and whose branches hold R each."""
+    L, d, H, dh, F = MODELS[model]
+    shape = ModelShape(L, d, H, dh, F, VOCAB, dtype, max_branches=N, max_rows_per_branch=T, max_shared=max(S, 1), max_private=R)
+    return VerifyContext(shape, _weights(model, dtype, gen, successor), DEVICE)
+
+
+def _fill(ctx, model, gen, N, S, R):
+    L, _, H, dh, _ = MODELS[model]
+    for l in range(L):
+        ks, vs = (_randn((H, S, dh), gen) if S else None for _ in range(2))
+        kp, vp = (_randn((N, H, R, dh), gen) if R else None for _ in range(2))
+        ctx.kv_load(l, ks, vs, kp, vp)
+    torch.cuda.synchronize()
+
+
+def _lens(gen, N, R, ragged):
+    if not ragged:
+        return torch.full((N,), R, dtype=torch.int32, device=DEVICE)
+    return torch.randint(R // 3, R + 1, (N,), generator=gen, device=DEVICE).to(torch.int32)
+
+
+def _uniform(gen, shape):
+    """Uniforms on the grid m * 2^-24 that the accept rule asks for."""
+    return torch.randint(0, 1 << 24, shape, generator=gen, device=DEVICE).float() * 2.0 ** -24
+
+
+def _guess(gen, tok, successor):
+    """What a draft model expects after `tok`: the target's own successor three times in four."""
+    other = torch.randint(0, VOCAB, tok.shape, generator=gen, device=DEVICE)
+    return torch.where(torch.rand(tok.shape, generator=gen, device=DEVICE) < 0.75, successor[tok], other)
+
+
+def _draft_row(gen, tok, successor):
+    """Draft distributions after the tokens `tok` [n]: float32 [n][V], peaked at the draft model's guess."""
+    z = _randn((tok.numel(), VOCAB), gen, 1.0, torch.float32)
+    peak = _randn((tok.numel(), 1), gen, 2.0, torch.float32).add_(GAP)
+    z.scatter_add_(1, _guess(gen, tok, successor)[:, None], peak)
+    return torch.softmax(z, dim=1)
+
+
+def _draft_chain(gen, pending, successor, gamma):
+    """(q [N][gamma][V], drafts [N][gamma]) of an autoregressive draft phase."""
+    tok, q, drafts = pending, [], []
+    for _ in range(gamma):
+        q.append(_draft_row(gen, tok, successor))
+        tok = torch.multinomial(q[-1], 1, generator=gen)[:, 0]
+        drafts.append(tok)
+    return torch.stack(q, 1).contiguous(), torch.stack(drafts, 1).to(torch.int32).contiguous()
+
+
+def _draft_tree(gen, pending, successor, ks):
+    """(q [N][n_par][V], tokens of all nodes [N][n_nodes]) of a candidate tree in level order."""
+    nodes, q, level = [pending[:, None]], [], pending[:, None]
+    for k in ks:
+        N, width = level.shape
+        rows = _draft_row(gen, level.reshape(-1), successor)
+        q.append(rows.view(N, width, VOCAB))
+        level = torch.multinomial(rows, k, replacement=True, generator=gen).view(N, width * k)
+        nodes.append(level)
+    return torch.cat(q, 1).contiguous(), torch.cat(nodes, 1).to(torch.int32).contiguous()
+
+
+def _ks(case):
+    return [int(k) for k in case["tree"].split(",")] if case.get("tree") else None
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device=DEVICE)
+    gen.manual_seed(seed)
+    kind, N = case["kind"], case["N"]
+    successor = _successors(gen)
+    pending = torch.randint(0, VOCAB, (N,), generator=gen, device=DEVICE)
+    st = dict(case=case)
+
+    if kind in ("verify", "accept"):
+        ks = _ks(case)
+        if ks:
+            q, nodes = _draft_tree(gen, pending, successor, ks)
+            T = tree_sizes(ks)[1]
+            rows, drafts = nodes[:, :T].contiguous(), nodes[:, 1:].contiguous()
+        else:
+            q, drafts = _draft_chain(gen, pending, successor, case["gamma"])
+            T = case["gamma"]
+            rows = torch.cat([pending[:, None].to(torch.int32), drafts[:, :T - 1]], 1).contiguous()
+        u_acc, u_res = _uniform(gen, tuple(drafts.shape)), _uniform(gen, (N,))
+        if kind == "accept":
+            p = _draft_row(gen, rows.reshape(-1).long(), successor).view(N, T, VOCAB)
+            st.update(p=torch.log(p) if case["logits"] else p, q=q, drafts=drafts, u_acc=u_acc, u_res=u_res)
+            return st
+        greedy = case["greedy"]
+        ctx = _context(case["model"], case["dtype"], gen, successor, N, T, case["S"], case["R"])
+        _fill(ctx, case["model"], gen, N, case["S"], case["R"])
+        plen = _lens(gen, N, case["R"], case["ragged"])
+        st.update(ctx=ctx, rows=rows, plen0=plen, plen=plen.clone(), k_config=ks,
+                  logits=torch.empty((N, T, VOCAB), dtype=torch.float32, device=DEVICE),
+                  accept=dict(q=None if greedy else q, draft_tok=drafts, u_acc=None if greedy else u_acc,
+                              u_res=None if greedy else u_res, temperature=case["temperature"], greedy=greedy))
+        return st
+
+    if kind == "draft":
+        ctx = _context(case["model"], case["dtype"], gen, successor, N, 1, case["S"], case["R"] + 1)
+        _fill(ctx, case["model"], gen, N, case["S"], case["R"])
+        plen = _lens(gen, N, case["R"], False)
+        st.update(ctx=ctx, rows=pending.to(torch.int32), plen0=plen, plen=plen.clone(), u=_uniform(gen, (N,)),
+                  logits=torch.empty((N, VOCAB), dtype=torch.float32, device=DEVICE),
+                  q=torch.empty((N, VOCAB), dtype=torch.float32, device=DEVICE))
+        return st
+
+    if kind == "prefill":
+        ctx = _context(case["model"], case["dtype"], gen, successor, N, case["gamma"], case["S"], case["gamma"])
+        st.update(ctx=ctx, prompt=torch.randint(0, VOCAB, (case["S"],), generator=gen, device=DEVICE).to(torch.int32),
+                  rows=pending.to(torch.int32).view(N, 1), plen=torch.zeros(N, dtype=torch.int32, device=DEVICE),
+                  logits=torch.empty((N, 1, VOCAB), dtype=torch.float32, device=DEVICE))
+        return st
+
+    # sched: target and draft contexts, each on a stream of its own
+    cap = case["new"] + 2 * case["gamma"]
+    S, G = case["S"], case["gamma"]
+    target_stream, draft_stream = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(target_stream):
+        target = _context(case["model"], "bf16", gen, successor, N, G, S, cap)
+        _fill(target, case["model"], gen, N, S, 0)
+    guess = _guess(gen, torch.arange(VOCAB, device=DEVICE), successor)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(draft_stream):
+        draft = _context("draft", "bf16", gen, guess, N, 1, S, cap)
+        _fill(draft, "draft", gen, N, S, 0)
+    n = case["new"] + G
+    st.update(target=target, draft=draft, first=pending.cpu().numpy().astype(np.int32), u=[_uniform(gen, (N, n)) for _ in range(3)],
+              plen_t=torch.zeros(N, dtype=torch.int32, device=DEVICE), plen_d=torch.zeros(N, dtype=torch.int32, device=DEVICE))
+    return st
+
+
+# ------------------------------------------------------------------------------------------------- one pass
+def run(st):
+    case = st["case"]
+    kind = case["kind"]
+    if kind == "verify":
+        st["plen"].copy_(st["plen0"])            # every pass sees the same context lengths
+        outs = st["ctx"].step(st["rows"], case["S"], st["plen"], flags=2 if case["greedy"] else 0, logits_out=st["logits"],
+                              accept=st["accept"], k_config=st["k_config"])
+        return [st["logits"], st["plen"]] + list(outs)
+    if kind == "draft":
+        st["plen"].copy_(st["plen0"])
+        tok = st["ctx"].draft_step(st["rows"], case["S"], st["plen"], st["u"], case["temperature"], q_out=st["q"],
+                                   logits_out=st["logits"])
+        return [tok, st["q"], st["logits"], st["plen"]]
+    if kind == "prefill":
+        n = st["ctx"].prefill_shared(st["prompt"])
+        st["ctx"].step(st["rows"], n, st["plen"], logits_out=st["logits"])
+        return [n, st["logits"]]
+    if kind == "accept":
+        return list(accept_resample(st["p"], st["q"], st["drafts"], st["u_acc"], st["u_res"], kind="logits" if case["logits"] else "probs",
+                                    temperature=case["temperature"], static_scratch=case["static"]))
+    st["plen_t"].zero_()
+    st["plen_d"].zero_()
+    tok, length, _ = sched_run(st["target"], st["draft"], st["first"], *st["u"], st["plen_t"], st["plen_d"], gamma=case["gamma"],
+                               max_new=case["new"], temperature=case["temperature"], shared_len_target=case["S"],
+                               shared_len_draft=case["S"], unit_branches=case["unit"])
+    return [tok, length, st["plen_t"]]
+
+
+# ------------------------------------------------------------------------------------------------- what a pass needs
+def _forward_work(model, dtype, rows, context_keys, seen_keys, head_rows):
+    """Bytes and flops of one forward over `rows` rows: every weight once, `context_keys` cached keys and values once,
+    the new ones written; `seen_keys` = key visits of all rows together."""
+    L, d, H, dh, F = MODELS[model]
+    layer, head = 4 * d * H * dh + 3 * d * F, VOCAB * d
+    per = {"bf16": 2.0, "bf16w8": 1.0, "bf16w4": 0.53125}[dtype]
+    kv = 4 * H * dh * L                                              # bytes of one token's keys and values
+    return ((L * layer + (head if head_rows else 0)) * per + (context_keys + rows) * kv + rows * d * 2 + head_rows * VOCAB * 4,
+            2.0 * rows * L * layer + 2.0 * head_rows * head + 4.0 * seen_keys * H * dh * L)
+
+
+def work(case):
+    kind, N = case["kind"], case["N"]
+    S, R = case.get("S", 0), case.get("R", 0)
+    if case.get("ragged"):
+        R = R * 2 / 3                                                # the mean of the drawn lengths
+    if kind == "accept":
+        cells = N * case["gamma"] * VOCAB
+        return {"bytes": 2 * cells * 4.0, "flops": 4.0 * cells}
+    if kind in ("verify", "draft"):
+        ks = _ks(case)
+        T = tree_sizes(ks)[1] if ks else case.get("gamma", 1)
+        nbytes, flops = _forward_work(case["model"], case["dtype"], N * T, S + N * R, N * T * (S + R + (T + 1) / 2), N * T)
+        return {"bytes": nbytes + (0 if case.get("greedy") else N * T * VOCAB * 4.0), "flops": flops}
+    if kind == "prefill":
+        a = _forward_work(case["model"], case["dtype"], S, 0, S * (S + 1) / 2, 0)
+        b = _forward_work(case["model"], case["dtype"], N, S, N * (S + 1), N)
+        return {"bytes": a[0] + b[0], "flops": a[1] + b[1]}
+    rounds = -(-case["new"] // case["gamma"])                        # every draft accepted
+    G = case["gamma"]
+    t = _forward_work(case["model"], "bf16", N * G, S, N * G * (S + case["new"] / 2), N * G)
+    q = _forward_work("draft", "bf16", N, S, N * (S + case["new"] / 2), N)
+    return {"bytes": rounds * (t[0] + G * q[0]), "flops": rounds * (t[1] + G * q[1])}
+
+
+def tolerance(case):
+    """About four times what the same rows differ by when they go through the library in another order of summation.
+
+    verify / draft: a step of 16 (8, 128) branches against one of its first 3 (2, 16) alone: logits 8e-6 .. 1.2e-5, p(x) up
+    to 6e-6; against a float64 model 7e-6 (7B, all 32 layers).  prefill: chunks of 96 rows against chunks of 24 rows, 8e-5
+    (a sum that moves in its last bits moves some cached keys and values to the next bfloat16).  accept: the two scratch
+    forms of the entry point, 6e-7.  Tokens and lengths: ties only."""
+    rel = {"verify": 6e-5, "draft": 6e-5, "prefill": 4e-4, "accept": 3e-6, "sched": 0.0}[case["kind"]]
+    return {"rel": rel, "differ": 0.01}
