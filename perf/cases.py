@@ -153,11 +153,11 @@ def _weights(model, dtype, gen, successor):
     return out
 
 
-def _context(model, dtype, gen, successor, N, T, S, R):
+def _context(make, model, dtype, gen, successor, N, T, S, R):
     """A context of the given capacities whose shared cache holds S synthetic tokens and whose branches hold R each."""
     L, d, H, dh, F = MODELS[model]
     shape = ModelShape(L, d, H, dh, F, VOCAB, dtype, max_branches=N, max_rows_per_branch=T, max_shared=max(S, 1), max_private=R)
-    return VerifyContext(shape, _weights(model, dtype, gen, successor), DEVICE)
+    return make(shape, _weights(model, dtype, gen, successor), DEVICE)
 
 
 def _fill(ctx, model, gen, N, S, R):
@@ -220,7 +220,7 @@ def _ks(case):
     return [int(k) for k in case["tree"].split(",")] if case.get("tree") else None
 
 
-def prepare(case, seed):
+def prepare(case, seed, make=VerifyContext):
     gen = torch.Generator(device=DEVICE)
     gen.manual_seed(seed)
     kind, N = case["kind"], case["N"]
@@ -244,7 +244,7 @@ def prepare(case, seed):
             st.update(p=torch.log(p) if case["logits"] else p, q=q, drafts=drafts, u_acc=u_acc, u_res=u_res)
             return st
         greedy = case["greedy"]
-        ctx = _context(case["model"], case["dtype"], gen, successor, N, T, case["S"], case["R"])
+        ctx = _context(make, case["model"], case["dtype"], gen, successor, N, T, case["S"], case["R"])
         _fill(ctx, case["model"], gen, N, case["S"], case["R"])
         plen = _lens(gen, N, case["R"], case["ragged"])
         st.update(ctx=ctx, rows=rows, plen0=plen, plen=plen.clone(), k_config=ks,
@@ -254,7 +254,7 @@ def prepare(case, seed):
         return st
 
     if kind == "draft":
-        ctx = _context(case["model"], case["dtype"], gen, successor, N, 1, case["S"], case["R"] + 1)
+        ctx = _context(make, case["model"], case["dtype"], gen, successor, N, 1, case["S"], case["R"] + 1)
         _fill(ctx, case["model"], gen, N, case["S"], case["R"])
         plen = _lens(gen, N, case["R"], False)
         st.update(ctx=ctx, rows=pending.to(torch.int32), plen0=plen, plen=plen.clone(), u=_uniform(gen, (N,)),
@@ -263,7 +263,7 @@ def prepare(case, seed):
         return st
 
     if kind == "prefill":
-        ctx = _context(case["model"], case["dtype"], gen, successor, N, case["gamma"], case["S"], case["gamma"])
+        ctx = _context(make, case["model"], case["dtype"], gen, successor, N, case["gamma"], case["S"], case["gamma"])
         st.update(ctx=ctx, prompt=torch.randint(0, VOCAB, (case["S"],), generator=gen, device=DEVICE).to(torch.int32),
                   rows=pending.to(torch.int32).view(N, 1), plen=torch.zeros(N, dtype=torch.int32, device=DEVICE),
                   logits=torch.empty((N, 1, VOCAB), dtype=torch.float32, device=DEVICE))
@@ -275,12 +275,12 @@ def prepare(case, seed):
     target_stream, draft_stream = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.stream(target_stream):
-        target = _context(case["model"], "bf16", gen, successor, N, G, S, cap)
+        target = _context(make, case["model"], "bf16", gen, successor, N, G, S, cap)
         _fill(target, case["model"], gen, N, S, 0)
     guess = _guess(gen, torch.arange(VOCAB, device=DEVICE), successor)
     torch.cuda.synchronize()
     with torch.cuda.stream(draft_stream):
-        draft = _context("draft", "bf16", gen, guess, N, 1, S, cap)
+        draft = _context(make, "draft", "bf16", gen, guess, N, 1, S, cap)
         _fill(draft, "draft", gen, N, S, 0)
     n = case["new"] + G
     st.update(target=target, draft=draft, first=pending.cpu().numpy().astype(np.int32), u=[_uniform(gen, (N, n)) for _ in range(3)],
@@ -351,6 +351,134 @@ def work(case):
     t = _forward_work(case["model"], "bf16", N * G, S, N * G * (S + case["new"] / 2), N * G)
     q = _forward_work("draft", "bf16", N, S, N * (S + case["new"] / 2), N)
     return {"bytes": rounds * (t[0] + G * q[0]), "flops": rounds * (t[1] + G * q[1])}
+
+
+# ------------------------------------------------------------------------------------------------- the same in 64 bits
+class _Plain:
+    """What a context is made of and holds, kept as plain tensors (it takes a VerifyContext's place in `prepare`)."""
+
+    def __init__(self, shape, weights, device):
+        self.weights, self.kv = weights, {}
+
+    def kv_load(self, layer, ks, vs, kp, vp):
+        self.kv[layer] = (ks, vs, kp, vp)
+
+
+def _wide(w, name, scale, dtype):
+    """A projection matrix in float64: a narrow one as the values that its codes stand for."""
+    m = w[name]
+    if dtype == "bf16":
+        return m.double()
+    if dtype == "bf16w8":
+        return m.view(torch.float8_e4m3fn).double() * w[scale].double()[:, None]
+    mags = torch.tensor([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0], dtype=torch.float64, device=DEVICE)
+    codes = torch.stack([m & 15, m >> 4], 2).view(m.shape[0], -1)
+    v = mags[(codes & 7).long()] * (1.0 - 2.0 * (codes >> 3).double())
+    return (v.view(m.shape[0], -1, 32) * torch.exp2(w[scale].double() - 127.0)[:, :, None]).view(m.shape[0], -1)
+
+
+def _rms(x, gain):
+    return x / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-5) * gain.double()
+
+
+def _rope(x, pos):
+    half = x.shape[2] // 2
+    ang = pos.double()[:, None] * 10000.0 ** (-torch.arange(half, dtype=torch.float64, device=DEVICE) / half)
+    c, s = torch.cos(ang)[:, None], torch.sin(ang)[:, None]
+    return torch.cat([x[..., :half] * c - x[..., half:] * s, x[..., half:] * c + x[..., :half] * s], 2)
+
+
+def _forward_exact(plain, model, dtype, tok, pos, attend):
+    """Logits of rows [M] at the positions `pos`; attend(layer, q, k, v [M][H][dh]) -> [M][H][dh]."""
+    L, d, H, dh, _ = MODELS[model]
+    w, M = plain.weights, tok.numel()
+    x = w["tok_emb"][tok.long()].double()
+    for l in range(L):
+        lw = w["layers"][l]
+        h = _rms(x, lw["norm_attn"])
+        q, k, v = ((h @ _wide(lw, n, "s" + n[1:], dtype).T).view(M, H, dh) for n in ("wq", "wk", "wv"))
+        x = x + attend(l, _rope(q, pos), _rope(k, pos), v).reshape(M, -1) @ _wide(lw, "wo", "so", dtype).T
+        h = _rms(x, lw["norm_ffn"])
+        gate, up = h @ _wide(lw, "wgate", "sgate", dtype).T, h @ _wide(lw, "wup", "sup", dtype).T
+        x = x + (gate * torch.sigmoid(gate) * up) @ _wide(lw, "wdown", "sdown", dtype).T
+    return _rms(x, w["norm_final"]) @ _wide(w, "lm_head", "lm_head_scale", dtype).T
+
+
+def _branch_attend(plain, S, plen, N, T, sees):
+    """Attention of N branches x T rows: the shared keys, the branch's private ones and the rows of its own that it sees."""
+    def attend(l, q, k, v):
+        ks, vs, kp, vp = plain.kv.get(l, (None,) * 4)
+        H, dh = q.shape[1:]
+        out = torch.empty_like(q)
+        for b in range(N):
+            r = slice(b * T, (b + 1) * T)
+            n = int(plen[b])
+            keys = ([ks[:, :S].double()] if S else []) + ([kp[b][:, :n].double()] if n else []) + [k[r].transpose(0, 1)]
+            vals = ([vs[:, :S].double()] if S else []) + ([vp[b][:, :n].double()] if n else []) + [v[r].transpose(0, 1)]
+            keys, vals = torch.cat(keys, 1), torch.cat(vals, 1)
+            score = torch.matmul(q[r].transpose(0, 1).contiguous(), keys.transpose(1, 2).contiguous()) / math.sqrt(dh)
+            score[:, :, S + n:].masked_fill_(~sees, -math.inf)
+            out[r] = torch.matmul(torch.softmax(score, 2), vals).transpose(0, 1)
+        return out
+    return attend
+
+
+def exact(case, seed):
+    """What `run` returns, from plain float64 (tokens and lengths, and what a tree's walk leaves, have no such value)."""
+    kind, N = case["kind"], case["N"]
+    if kind == "sched":
+        return None
+    st = prepare(case, seed, make=_Plain)
+    if kind == "accept":
+        p = st["p"].double()
+        p = torch.softmax(p / case["temperature"], 2) if case["logits"] else p
+        return [None, None, None, p.gather(2, st["drafts"].long()[:, :, None])[:, :, 0]]
+    plain, model, dtype, S = st["ctx"], case["model"], case["dtype"], case["S"]
+    _, _, H, dh, _ = MODELS[model]
+    if kind == "prefill":
+        # the prompt's rows see each other through the cache, which holds bfloat16
+        n, cache = st["prompt"].numel(), {}
+
+        def attend(l, q, k, v):
+            cache[l] = k, v = k.to(torch.bfloat16).transpose(0, 1).contiguous(), v.to(torch.bfloat16).transpose(0, 1).contiguous()
+            out = torch.empty_like(q)
+            later = torch.ones((n, n), dtype=torch.bool, device=DEVICE).triu(1)
+            for h in range(H):
+                score = (q[:, h] @ k[h].double().T / math.sqrt(dh)).masked_fill_(later, -math.inf)
+                out[:, h] = torch.softmax(score, 1) @ v[h].double()
+            return out
+        _forward_exact(plain, model, dtype, st["prompt"], torch.arange(n, device=DEVICE), attend)
+        plain.kv = {l: (k, v, None, None) for l, (k, v) in cache.items()}
+    T = st["rows"].numel() // N
+    ks = _ks(case)
+    level, parent = [0], [0]                                          # of every node of a branch, in level order
+    first, width = 0, 1
+    for k in ks or [1] * (T - 1):
+        parent += [first + i // k for i in range(width * k)]
+        first, width = first + width, width * k
+        level += [level[first - 1] + 1] * width
+    sees = torch.zeros((T, T), dtype=torch.bool, device=DEVICE)
+    for j in range(T):
+        i = j
+        sees[j, 0] = True
+        while i:
+            sees[j, i] = True
+            i = parent[i]
+    depth = torch.tensor(level[:T], device=DEVICE)
+    plen = st.get("plen0", st["plen"])
+    pos = (S + plen[:, None] + depth[None, :]).reshape(-1)
+    logits = _forward_exact(plain, model, dtype, st["rows"].reshape(-1), pos, _branch_attend(plain, S, plen.tolist(), N, T, sees))
+    if kind == "prefill":
+        return [None, logits.view(N, 1, VOCAB)]
+    p = torch.softmax(logits / case["temperature"], 1)
+    if kind == "draft":
+        return [None, p, logits, None]
+    logits = logits.view(N, T, VOCAB)
+    if ks:
+        return [logits, None, None, None, None, None, None]
+    drafts = st["accept"]["draft_tok"].long()
+    p_tok = torch.zeros_like(drafts, dtype=torch.float64) if case["greedy"] else p.view(N, T, VOCAB).gather(2, drafts[:, :, None])[:, :, 0]
+    return [logits, None, None, None, None, p_tok]
 
 
 def tolerance(case):
