@@ -60,7 +60,6 @@ int expand_tree(const seed_tree *t, TreeInfo *out) {
 
 namespace {
 
-constexpr int kMaxCounters = 4096;
 constexpr int kMaxAttnSlots = 128;
 constexpr int kMaxHeads = 1024;
 
@@ -154,24 +153,26 @@ Layout make_layout(const seed_model_cfg &c) {
     // one layer's weights
     size_t lo = 0;
     auto ltake = [&](size_t bytes) { size_t o = lo; lo = align_up(lo + bytes, 256); return o; };
-    L.w_qkv = ltake(3 * HD * d * wbits / 8);
-    L.w_o = ltake(d * HD * wbits / 8);
-    L.w_gu = ltake(2 * F * d * wbits / 8);
-    L.w_d = ltake(d * F * wbits / 8);
+    // (narrow weights are packed in pairs of k-tiles of 32 inputs: K rounded up to 64)
+    const size_t kd = w8 || w4 ? align_up(d, 64) : d, kHD = w8 || w4 ? align_up(HD, 64) : HD, kF = w8 || w4 ? align_up(F, 64) : F;
+    L.w_qkv = ltake(3 * HD * kd * wbits / 8);
+    L.w_o = ltake(d * kHD * wbits / 8);
+    L.w_gu = ltake(2 * F * kd * wbits / 8);
+    L.w_d = ltake(d * kF * wbits / 8);
     // (one-byte weights: per-output-row scales, in the order of the packed tiles; four-bit weights: one scale
     // byte per output row and 32 inputs)
-    L.s_qkv = ltake(w8 ? 3 * HD * 4 : w4 ? 3 * HD * d / 32 : 0);
-    L.s_o = ltake(w8 ? d * 4 : w4 ? d * HD / 32 : 0);
-    L.s_gu = ltake(w8 ? 2 * F * 4 : w4 ? 2 * F * d / 32 : 0);
-    L.s_d = ltake(w8 ? d * 4 : w4 ? d * F / 32 : 0);
+    L.s_qkv = ltake(w8 ? 3 * HD * 4 : w4 ? 3 * HD * kd / 32 : 0);
+    L.s_o = ltake(w8 ? d * 4 : w4 ? d * kHD / 32 : 0);
+    L.s_gu = ltake(w8 ? 2 * F * 4 : w4 ? 2 * F * kd / 32 : 0);
+    L.s_d = ltake(w8 ? d * 4 : w4 ? d * kF / 32 : 0);
     L.g_attn = ltake(d * L.es);
     L.g_ffn = ltake(d * L.es);
     L.layer_stride = lo;
     L.layers0 = take(L.layer_stride * c.n_layers);
     L.emb = take(V * d * L.es);
     L.g_final = take(d * L.es);
-    L.lm = take(V * d * wbits / 8);
-    L.s_lm = take(w8 ? V * 4 : w4 ? V * d / 32 : 256);
+    L.lm = take(V * kd * wbits / 8);
+    L.s_lm = take(w8 ? V * 4 : w4 ? V * kd / 32 : 256);
     L.ks_stride = align_up(H * L.cap_s * dh * L.es, 256);
     L.kp_stride = align_up((size_t)c.max_branches * H * L.cap_p * dh * L.es, 256);
     L.ks = take(L.ks_stride * c.n_layers);
@@ -191,7 +192,7 @@ Layout make_layout(const seed_model_cfg &c) {
     L.qkv = take((size_t)L.M_cap * 3 * HD * 4);
     L.rinv = take((size_t)L.Mp_cap * 4);
     L.ssq = take((size_t)L.M_cap * (d / 16 + 1) * 4);
-    L.counters = take(4096 * 4);
+    L.counters = take(kMaxGemmCounters * 4);
     L.attn_counters = take(kMaxHeads * 4);
     L.n_pos = c.max_shared + c.max_private + c.max_rows_per_branch + 1;
     L.rope = take((size_t)L.n_pos * dh * 4);
@@ -326,7 +327,6 @@ int run_forward_bf16(seed_ctx *c, int N, int T, int S, int prefill_shared, const
     hipStream_t st = c->stream;
     const int M = N * T, Mp = round_up(M, 16), Mq = round_up(M, 32);
     const int d = g.d_model, F = g.d_ff, H = g.n_heads, dh = g.head_dim, HD = L.HD, V = g.vocab;
-    const int m_tiles = Mp / 16;
     float *x = (float *)at(c, L.x);
     float *ssq = (float *)at(c, L.ssq);
     int32_t *status = (int32_t *)at(c, L.status);
@@ -345,15 +345,7 @@ int run_forward_bf16(seed_ctx *c, int N, int T, int S, int prefill_shared, const
         a.part_floats = L.part_floats;
         a.counters = (int *)at(c, L.counters);
         a.eps = g.rms_eps;
-        int wn, wk, tn, sk, wide, ms;
-        gemm_bf16_pick(a.NT, a.KT, epi, m_tiles, &wn, &wk, &tn, &sk, &wide, &ms, c->w8 || c->w4);
-        while (sk > 1 && (size_t)sk * M * Nout > L.part_floats) --sk;
-        a.SK = sk;
-        if (sk > 1 && (a.NT / (wn * tn) + 8) * ms + 2 > kMaxCounters) {
-            set_error("projection with %d column groups exceeds the counter array", a.NT / (wn * tn));
-            return SEED_E_CAPACITY;
-        }
-        return profiled(c, (double)Nout * K * (c->w4 ? 0.53125 : c->w8 ? 1.0 : 2.0), [&]() { return launch_gemm_bf16(a, epi, m_tiles, st); });
+        return profiled(c, (double)Nout * K * (c->w4 ? 0.53125 : c->w8 ? 1.0 : 2.0), [&]() { return launch_gemm_bf16(a, epi, st); });
     };
 
     int ks_shared = 1, keys_per_range = 32, ks_priv = 0, keys_per_range_priv = 128;

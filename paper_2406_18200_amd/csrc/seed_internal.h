@@ -71,14 +71,15 @@ struct GemmArgs {
     float *ssq;            // RESID: [M][NT] per-tile sums of squares of the new residual stream (out)
     float eps;
     const float *w_scale;  // 8-bit weights: one float per output feature, in packed tile order (NULL: bf16 weights)
-    const uint8_t *w_mx;   // 4-bit weights: E8M0 block scales [n-tile][k-tile][16] (NULL otherwise)
+    const uint8_t *w_mx;   // 4-bit weights: E8M0 block scales [n-tile][pair of k-tiles][16][2] (NULL otherwise)
     int rot;               // multiplier of the per-column-group rotation of the k walk (0: none)
     int MS;                // row splits: MS workgroups per column group, each with 1 / MS of the row tiles (0 or 1: none)
 };
-void gemm_bf16_pick(int NT, int KT, int epi, int m_tiles, int *wn, int *wk, int *tn, int *sk, int *wide, int *ms,
-                    int w8);
-int launch_gemm_bf16_cfg(const GemmArgs &a, int epi, int m_tiles, int wn, int wk, int tn, int wide, hipStream_t st);
-int launch_gemm_bf16(GemmArgs a, int epi, int m_tiles, hipStream_t st);   // a.SK < 1: pick automatically
+constexpr int kMaxGemmCounters = 4096;        // ints of GemmArgs::counters
+int launch_gemm_bf16(GemmArgs a, int epi, hipStream_t st);   // chooses form, shape and split (SK, MS, kt_per_split, rot)
+int launch_gemm_stream_w16(const GemmArgs &a, int epi, int tm, int tn, dim3 grid, hipStream_t st);
+int launch_gemm_stream_w8(const GemmArgs &a, int epi, int tm, int tn, dim3 grid, hipStream_t st);
+int launch_gemm_stream_w4(const GemmArgs &a, int epi, int tm, int tn, dim3 grid, hipStream_t st);
 int launch_pack_weight(const void *W, void *dst, int n_rows, int K, int dst_tile0, int dst_tile_step,
                        hipStream_t st);
 int launch_pack_weight8(const void *codes, const float *scale, void *dst, float *scale_dst, int n_rows, int K,
