@@ -262,6 +262,12 @@ int seed_accept_resample(const seed_accept_args *args, void *hip_stream);
  */
 int seed_accept_resample_static(const seed_accept_args *args, void *hip_stream);
 
+/* seed_accept_resample with scratch memory of the caller (device, 16-byte aligned, seed_accept_scratch_bytes bytes, used
+ * until the call's work on the stream is done): the softmax statistics of the target rows then come from a launch
+ * that fills the GPU instead of from the one workgroup per branch. */
+size_t seed_accept_scratch_bytes(int32_t n_branches, int32_t n_target_rows);
+int seed_accept_resample_ws(const seed_accept_args *args, void *scratch, size_t scratch_bytes, void *hip_stream);
+
 /*
  * Stateless draw x ~ probs rows by the fixed-point inverse CDF (the draft-side sampler of Section 3.1).
  * probs: n_rows rows of V floats, row i at probs + i * row_stride; u: [n_rows]; tok_out: [n_rows].

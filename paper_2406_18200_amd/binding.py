@@ -95,7 +95,7 @@ class SchedArgsC(C.Structure):
 
 
 EXPORTS = ("seed_verify_workspace_bytes", "seed_verify_init", "seed_verify_step", "seed_draft_step",
-           "seed_accept_resample", "seed_accept_resample_static", "seed_sample_probs", "seed_uniform_philox", "seed_kv_load", "seed_verify_status",
+           "seed_accept_resample", "seed_accept_resample_static", "seed_accept_scratch_bytes", "seed_accept_resample_ws", "seed_sample_probs", "seed_uniform_philox", "seed_kv_load", "seed_verify_status",
            "seed_verify_profile_enable", "seed_verify_profile_read", "seed_verify_profile_overhead", "seed_hbm_read_probe",
            "seed_verify_destroy", "seed_last_error",
            "seed_sched_workspace_bytes", "seed_sched_run")
@@ -123,6 +123,9 @@ def load_library():
     lib.seed_draft_step.argtypes = [C.c_void_p, C.POINTER(DraftArgsC)]
     lib.seed_accept_resample.argtypes = [C.POINTER(AcceptArgsC), C.c_void_p]
     lib.seed_accept_resample_static.argtypes = [C.POINTER(AcceptArgsC), C.c_void_p]
+    lib.seed_accept_scratch_bytes.restype = C.c_size_t
+    lib.seed_accept_scratch_bytes.argtypes = [C.c_int32, C.c_int32]
+    lib.seed_accept_resample_ws.argtypes = [C.POINTER(AcceptArgsC), C.c_void_p, C.c_size_t, C.c_void_p]
     lib.seed_sample_probs.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
     lib.seed_uniform_philox.argtypes = [C.c_uint32, C.c_uint32, C.c_void_p, C.c_int64, C.c_void_p]
     lib.seed_kv_load.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
@@ -217,8 +220,15 @@ def accept_resample(p_or_logits, q, draft_tok, u_acc, u_res, *, kind="probs", te
         outs = _accept_outputs(N, gamma, p_or_logits.device, n_drafts=draft_tok.shape[1])
     a = _accept_struct(N, gamma, Tp, V, SEED_KIND_LOGITS if kind == "logits" else SEED_KIND_PROBS, greedy,
                        temperature, p_or_logits, q, draft_tok, u_acc, u_res, *outs[:4], private_len, tree, path)
-    fn = lib.seed_accept_resample_static if static_scratch else lib.seed_accept_resample
-    _check(fn(C.byref(a), _stream_handle()))
+    if static_scratch:
+        _check(lib.seed_accept_resample_static(C.byref(a), _stream_handle()))
+    elif (kind == "logits" or greedy) and N * Tp > 0:
+        # softmax statistics are wanted: scratch for them from the caching allocator, on the stream of the call
+        nbytes = lib.seed_accept_scratch_bytes(N, Tp)
+        scratch = torch.empty(nbytes, dtype=torch.uint8, device=p_or_logits.device)
+        _check(lib.seed_accept_resample_ws(C.byref(a), _ptr(scratch), nbytes, _stream_handle()))
+    else:
+        _check(lib.seed_accept_resample(C.byref(a), _stream_handle()))
     del keep
     return outs if path is None else tuple(outs[:4]) + (path,)
 

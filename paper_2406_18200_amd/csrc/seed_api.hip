@@ -694,6 +694,27 @@ int seed_accept_resample(const seed_accept_args *args, void *hip_stream) {
     return launch_accept(*args, nullptr, nullptr, 0, nullptr, (hipStream_t)hip_stream);
 }
 
+size_t seed_accept_scratch_bytes(int32_t n_branches, int32_t n_target_rows) {
+    if (n_branches < 0 || n_target_rows < 1 || (int64_t)n_branches * n_target_rows > INT32_MAX) return 0;
+    return accept_scratch_bytes(n_branches * n_target_rows);
+}
+
+int seed_accept_resample_ws(const seed_accept_args *args, void *scratch, size_t scratch_bytes, void *hip_stream) {
+    int rc = check_accept_args(args);
+    if (rc) return rc;
+    if (args->n_branches == 0) return SEED_OK;
+    if (scratch == nullptr) { set_error("accept: scratch is NULL"); return SEED_E_NULL_PTR; }
+    if (((uintptr_t)scratch & 15) != 0) { set_error("accept: scratch must be 16-byte aligned"); return SEED_E_INVALID_ARG; }
+    const size_t need = seed_accept_scratch_bytes(args->n_branches, args->n_target_rows);
+    if (need == 0 || scratch_bytes < need) { set_error("accept: scratch too small: %zu < %zu", scratch_bytes, need); return SEED_E_CAPACITY; }
+    if (args->tree != nullptr) {
+        TreeInfo ti;
+        if ((rc = expand_tree(args->tree, &ti))) return rc;
+        return launch_accept_tree(*args, ti, scratch, nullptr, 0, nullptr, nullptr, (hipStream_t)hip_stream);
+    }
+    return launch_accept(*args, scratch, nullptr, 0, nullptr, (hipStream_t)hip_stream);
+}
+
 int seed_accept_resample_static(const seed_accept_args *args, void *hip_stream) {
     int rc = check_accept_args(args);
     if (rc) return rc;
