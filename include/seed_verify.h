@@ -233,6 +233,11 @@ typedef struct {
 /* Bytes of device workspace a context needs: repacked weights + KV caches + activations. 0 on error. */
 size_t seed_verify_workspace_bytes(const seed_model_cfg *cfg);
 
+/* Takes a prompt into the shared cache: n_tokens device-resident token ids that follow the shared_len tokens already
+ * there.  The same as SEED_STEP_PREFILL_SHARED steps over the whole prompt, in chunks as large as the context's
+ * workspace allows (bf16 contexts: up to 2048 rows, whatever max_branches and max_rows_per_branch are). */
+int seed_prefill_shared(seed_ctx *ctx, const int32_t *tokens, int32_t n_tokens, int32_t shared_len);
+
 /*
  * Create a context.  Validates cfg, carves `workspace` (device memory, 256-byte aligned, at least
  * seed_verify_workspace_bytes(cfg)), repacks the weights into it (the caller's weight tensors may be

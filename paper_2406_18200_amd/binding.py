@@ -94,7 +94,7 @@ class SchedArgsC(C.Structure):
                 ("stats", C.POINTER(SchedStatsC))]
 
 
-EXPORTS = ("seed_verify_workspace_bytes", "seed_verify_init", "seed_verify_step", "seed_draft_step",
+EXPORTS = ("seed_verify_workspace_bytes", "seed_verify_init", "seed_verify_step", "seed_prefill_shared", "seed_draft_step",
            "seed_accept_resample", "seed_accept_resample_static", "seed_accept_scratch_bytes", "seed_accept_resample_ws", "seed_sample_probs", "seed_uniform_philox", "seed_kv_load", "seed_verify_status",
            "seed_verify_profile_enable", "seed_verify_profile_read", "seed_verify_profile_overhead", "seed_hbm_read_probe",
            "seed_verify_destroy", "seed_last_error",
@@ -126,6 +126,7 @@ def load_library():
     lib.seed_accept_scratch_bytes.restype = C.c_size_t
     lib.seed_accept_scratch_bytes.argtypes = [C.c_int32, C.c_int32]
     lib.seed_accept_resample_ws.argtypes = [C.POINTER(AcceptArgsC), C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.seed_prefill_shared.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32]
     lib.seed_sample_probs.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
     lib.seed_uniform_philox.argtypes = [C.c_uint32, C.c_uint32, C.c_void_p, C.c_int64, C.c_void_p]
     lib.seed_kv_load.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
@@ -341,14 +342,12 @@ class VerifyContext:
         return outs
 
     def prefill_shared(self, tokens, shared_len=0):
-        """Appends prefix tokens (int32 device tensor [S]) to the shared KV cache in chunks; returns new length."""
-        cap = self.shape.max_branches * self.shape.max_rows_per_branch
-        pos = int(shared_len)
-        for lo in range(0, tokens.numel(), cap):
-            chunk = tokens[lo:lo + cap].contiguous().view(1, -1)
-            self.step(chunk, pos, None, flags=SEED_STEP_PREFILL_SHARED)
-            pos += chunk.shape[1]
-        return pos
+        """Appends prefix tokens (int32 device tensor [S]) to the shared KV cache; returns the new length."""
+        n = tokens.numel()
+        if n:
+            tokens = tokens.contiguous()
+            _check(self.lib.seed_prefill_shared(self.handle, _ptr(tokens), n, int(shared_len)))
+        return int(shared_len) + n
 
     def draft_step(self, row_tok, shared_len, private_len, u, temperature, *, q_out=None, tok_out=None,
                    q_stride=None, tok_stride=1, flags=0, logits_out=None, branch_slot=None):

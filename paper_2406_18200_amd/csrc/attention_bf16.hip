@@ -944,8 +944,10 @@ __global__ __launch_bounds__(256, 2) void attn_partial_kernel(AttnParams P) {
         h = unit / P.ks_shared;
         const int total = P.prefill_shared ? P.S + P.M : P.S;
         const int kbeg = ks * P.keys_per_range;
-        const int kend = min(total, kbeg + P.keys_per_range);
         const int grp0 = quad * P.gpw;
+        // (prefill: the keys past the task's last row are seen by none of its rows)
+        const int seen = P.prefill_shared ? min(total, P.S + 16 * min(grp0 + P.gpw, P.n_groups)) : total;
+        const int kend = min(seen, kbeg + P.keys_per_range);
         attn_task_lds<DH, FUSED, TREE>(P, h, grp0, min(P.gpw, P.n_groups - grp0), P.k_shared + (size_t)h * P.cap_s * DH,
                                  P.vt_shared + (size_t)h * DH * P.cap_s, kbeg, max(kbeg, kend),
                                  P.prefill_shared ? P.S + 1 : P.S, P.prefill_shared ? 1 : 0, ks, smem);
@@ -1055,6 +1057,17 @@ void attn_bf16_plan(int M, int H, int N, int total_shared_keys, int cap_priv_key
     const int per_units = (units + ks - 1) / ks;
     *ks_shared = (units + per_units - 1) / per_units;
     *keys_per_range = per_units * unit;
+}
+
+int attn_bf16_prefill_slots(int M, int H, int max_keys) {
+    // (attn_bf16_plan's bound before it evens out the ranges, which only lowers their number)
+    const int n_groups = (M + 15) / 16;
+    const bool lds_tasks = n_groups > 1;
+    const int unit = lds_tasks ? 64 : 128, units = (max_keys + unit - 1) / unit, base = lds_tasks ? H * ((n_groups + 3) / 4) : H;
+    const int want = ((lds_tasks ? 448 : 512) + base - 1) / base;
+    int most = want < units ? want : units;
+    if (lds_tasks && most < (units + 15) / 16) most = (units + 15) / 16;
+    return most < 1 ? 1 : most > 32 ? 32 : most;
 }
 
 int launch_attn_bf16(const AttnBf16Args &a, hipStream_t st) {

@@ -632,7 +632,7 @@ GemmPlan gemm_plan(int NT, int KT, int epi, int M, int wb, size_t part_floats) {
     // Split-K partials cost a round trip through memory.  All in units of 1/16 KiB through one CU.
     static const int kStore[] = {1, 2, 3, 4, 6, 8, 0}, kResid[] = {1, 2, 4, 5, 8, 0}, kSwiglu[] = {2, 4, 6, 8, 0};
     long best = -1;
-    const int ms0 = (m_tiles + 5) / 6, ms1 = (m_tiles + 1) / 2;
+    const int ms0 = (m_tiles + 5) / 6, ms1 = (m_tiles + 1) / 2 < ms0 + 3 ? (m_tiles + 1) / 2 : ms0 + 3;
     for (int ms = ms0; ms <= ms1; ++ms) {
         const int tm = (m_tiles + ms - 1) / ms;
         if ((m_tiles + tm - 1) / tm != ms) continue;      // (a share would be empty)

@@ -68,14 +68,16 @@ inline int round_up(int v, int a) { return (v + a - 1) / a * a; }
 
 struct Layout {
     size_t es;                    // bytes per weight / KV element
-    int HD, M_cap, Mp_cap, Mq_cap, cap_s, cap_p;
+    int HD, M_cap, Mq_cap, cap_s, cap_p;
+    int R_cap, Rp_cap, Rq_cap;    // rows of a launch sequence: a step's, or a prefill chunk's where that is more
+    size_t attn_rows;             // partial rows (slots x rows rounded up to 32) the attention may leave
     // weights
     size_t w_qkv, w_o, w_gu, w_d, s_qkv, s_o, s_gu, s_d, g_attn, g_ffn, layer_stride, layers0;
     size_t emb, g_final, lm, s_lm;
     // KV caches (per-layer strides)
     size_t ks, vs, kp, vp, ks_stride, kp_stride;
     // activations
-    size_t x, act_d, act_hd, act_f, part, qkv, rinv, ssq, counters, attn_counters, rope, q, o_part, ml_part, logits, acc_stats, draft_counters, status,
+    size_t x, act_d, act_hd, act_f, part, qkv, ssq, counters, attn_counters, rope, q, o_part, ml_part, logits, acc_stats, draft_counters, status,
         tree_depth, tree_anc, commit_rows;
     int n_pos;
     size_t part_floats;
@@ -144,8 +146,14 @@ Layout make_layout(const seed_model_cfg &c) {
     L.HD = (int)(H * dh);
     const size_t HD = L.HD;
     L.M_cap = c.max_branches * c.max_rows_per_branch;
-    L.Mp_cap = round_up(L.M_cap, 16);
     L.Mq_cap = round_up(L.M_cap, 32);
+    L.R_cap = L.M_cap;
+    if (bf) {
+        const int chunk = c.max_shared < kMaxPrefillRows ? c.max_shared : kMaxPrefillRows;
+        if (chunk > L.R_cap) L.R_cap = chunk;
+    }
+    L.Rp_cap = round_up(L.R_cap, 16);
+    L.Rq_cap = round_up(L.R_cap, 32);
     L.cap_s = round_up(c.max_shared > 0 ? c.max_shared : 1, 32);
     L.cap_p = round_up(c.max_private + c.max_rows_per_branch, 32);
     size_t off = 0;
@@ -182,23 +190,28 @@ Layout make_layout(const seed_model_cfg &c) {
     size_t widest = 3 * HD;
     if (2 * F > widest) widest = 2 * F;
     if (d > widest) widest = d;
-    L.x = take((size_t)L.Mp_cap * d * 4);
-    L.act_d = take((size_t)L.Mp_cap * d * 4);             // bf16 path: hi + lo halves; fp32 path: plain floats
-    L.act_hd = take((size_t)L.Mp_cap * HD * 4);
-    L.act_f = take((size_t)L.Mp_cap * F * 4);
+    L.x = take((size_t)L.Rp_cap * d * 4);
+    L.act_d = take((size_t)L.Rp_cap * d * 4);             // bf16 path: hi + lo halves; fp32 path: plain floats
+    L.act_hd = take((size_t)L.Rp_cap * HD * 4);
+    L.act_f = take((size_t)L.Rp_cap * F * 4);
     // split-K partials: SK * Nout stays near 384 workgroups * 128 columns; V covers an unsplit LM head
     L.part_floats = (size_t)L.M_cap * (bf ? (widest > 65536 ? widest : 65536) : widest);
     L.part = take(L.part_floats * 4);
-    L.qkv = take((size_t)L.M_cap * 3 * HD * 4);
-    L.rinv = take((size_t)L.Mp_cap * 4);
-    L.ssq = take((size_t)L.M_cap * (d / 16 + 1) * 4);
+    L.qkv = take((size_t)L.R_cap * 3 * HD * 4);
+    L.ssq = take((size_t)L.R_cap * (d / 16 + 1) * 4);
     L.counters = take(kMaxGemmCounters * 4);
     L.attn_counters = take(kMaxHeads * 4);
     L.n_pos = c.max_shared + c.max_private + c.max_rows_per_branch + 1;
     L.rope = take((size_t)L.n_pos * dh * 4);
-    L.q = take((size_t)L.Mq_cap * HD * 4);   // bf16 path: hi and lo planes
-    L.o_part = take(bf ? (size_t)kMaxAttnSlots * L.Mq_cap * HD * 4 : 256);
-    L.ml_part = take(bf ? (size_t)kMaxAttnSlots * L.Mq_cap * H * 2 * 4 : 256);
+    L.q = take((size_t)L.Rq_cap * HD * 4);   // bf16 path: hi and lo planes
+    L.attn_rows = (size_t)kMaxAttnSlots * L.Mq_cap;
+    if (bf)
+        for (int m = 16; m < L.R_cap + 16; m += 16) {
+            const size_t rows = (size_t)attn_bf16_prefill_slots(m, c.n_heads, c.max_shared) * round_up(m, 32);
+            if (rows > L.attn_rows) L.attn_rows = rows;
+        }
+    L.o_part = take(bf ? L.attn_rows * HD * 4 : 256);
+    L.ml_part = take(bf ? L.attn_rows * H * 2 * 4 : 256);
     L.logits = take((size_t)L.M_cap * V * 4);
     L.acc_stats = take(accept_scratch_bytes(L.M_cap));
     L.draft_counters = take((size_t)L.M_cap * 4);
@@ -330,7 +343,7 @@ int run_forward_bf16(seed_ctx *c, int N, int T, int S, int prefill_shared, const
     float *x = (float *)at(c, L.x);
     float *ssq = (float *)at(c, L.ssq);
     int32_t *status = (int32_t *)at(c, L.status);
-    const size_t q_plane = (size_t)L.Mq_cap * HD;
+    const size_t q_plane = (size_t)L.Rq_cap * HD;
     int rc;
 
     auto gemm = [&](int epi, const void *W, const void *scale, int Nout, int K, const void *Xp, GemmArgs a) -> int {
@@ -353,6 +366,10 @@ int run_forward_bf16(seed_ctx *c, int N, int T, int S, int prefill_shared, const
                    &ks_priv, &keys_per_range_priv);
     if (ks_shared + ks_priv + 1 > kMaxAttnSlots) {
         set_error("attention plan needs %d partial slots (max %d)", ks_shared + ks_priv + 1, kMaxAttnSlots);
+        return SEED_E_CAPACITY;
+    }
+    if ((size_t)(prefill_shared ? ks_shared : ks_shared + ks_priv + 1) * Mq > L.attn_rows) {
+        set_error("attention plan needs %d partial slots of %d rows (the workspace holds %zu rows)", ks_shared, Mq, L.attn_rows);
         return SEED_E_CAPACITY;
     }
 
@@ -833,6 +850,27 @@ int seed_verify_step(seed_ctx *c, const seed_step_args *a) {
                              c->stream);
     if (a->flags & SEED_STEP_COMMIT_ALL)
         return launch_add_len(a->private_len, N, T, a->branch_slot, g.max_branches, c->stream);
+    return SEED_OK;
+}
+
+int seed_prefill_shared(seed_ctx *c, const int32_t *tokens, int32_t n_tokens, int32_t shared_len) {
+    if (c == nullptr) { set_error("context is NULL"); return SEED_E_NOT_INIT; }
+    if (n_tokens < 0 || shared_len < 0) { set_error("prefill: need n_tokens >= 0, shared_len >= 0"); return SEED_E_INVALID_ARG; }
+    if (n_tokens == 0) return SEED_OK;
+    if (tokens == nullptr) { set_error("prefill: tokens is NULL"); return SEED_E_NULL_PTR; }
+    if ((int64_t)shared_len + n_tokens > c->cfg.max_shared) {
+        set_error("prefill: shared_len %d + %d tokens exceeds max_shared %d", shared_len, n_tokens, c->cfg.max_shared);
+        return SEED_E_CAPACITY;
+    }
+    // chunks of equal size (rounded up to whole row tiles), as few as the workspace allows
+    const int n_chunks = (n_tokens + c->L.R_cap - 1) / c->L.R_cap;
+    int chunk = round_up((n_tokens + n_chunks - 1) / n_chunks, 16);
+    if (chunk > c->L.R_cap) chunk = c->L.R_cap;
+    for (int lo = 0; lo < n_tokens; lo += chunk) {
+        const int rows = n_tokens - lo < chunk ? n_tokens - lo : chunk;
+        const int rc = run_forward(c, 1, rows, shared_len + lo, 1, tokens + lo, nullptr, nullptr, nullptr, nullptr);
+        if (rc) return rc;
+    }
     return SEED_OK;
 }
 

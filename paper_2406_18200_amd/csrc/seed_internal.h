@@ -30,6 +30,9 @@ int expand_tree(const seed_tree *t, TreeInfo *out);   // validates; SEED_OK or a
 // Most rows (branches x rows per branch) of one bf16 step: 48 row tiles, run as row shares of three or four
 // tiles that share a weight pass.
 constexpr int kMaxStepRows = 768;
+// Most prompt rows of one prefill chunk.  A chunk's weights are read once for all its rows, so it is as large as its
+// activations (about 160 KiB a row at the 7B shapes) and attention partials can reasonably be.
+constexpr int kMaxPrefillRows = 2048;
 
 // ---- accept.hip ------------------------------------------------------------------------------
 size_t accept_scratch_bytes(int max_rows);
@@ -113,6 +116,8 @@ int launch_add_len(int32_t *len, int n, int delta, const int32_t *branch_slot, i
 // ---- attention_bf16.hip ----------------------------------------------------------------------------
 void attn_bf16_plan(int M, int H, int N, int total_shared_keys, int cap_priv_keys, int prefill_shared,
                     int *ks_shared, int *keys_per_range, int *ks_priv, int *keys_per_range_priv);
+// most key ranges a prefill chunk of M rows gets with at most max_keys keys
+int attn_bf16_prefill_slots(int M, int H, int max_keys);
 // Verify / decode steps (prefill_shared == 0) run as one launch that reads qkv / rope directly, appends to the
 // private cache, sets status bit 0 on a private-length overflow and merges through `counters` (n_heads ints,
 // zero on entry, left zero); the shared-prefix prefill reads q (hi/lo planes) written by launch_rope_kv.
