@@ -584,21 +584,24 @@ GemmPlan gemm_plan(int NT, int KT, int epi, int M, int wb, size_t part_floats) {
     if (m_tiles > 8 && NT % 4 == 0 && KT >= 64 && wb == 16) {
         // Past 128 rows the launch is bound by MFMA issue and LDS reads, not by memory, so the big register tiles of
         // the wide form: up to eight row tiles x four n-tiles per wavefront (a weight fragment feeds up to 16 MFMAs,
-        // an activation fragment read from LDS four); 4 x 2 wavefronts for wide outputs, 2 x 4 (eight n-tiles per
-        // workgroup, K split four ways inside it) for narrow ones.  One such workgroup fills a CU, so the launch runs
-        // in whole rounds of 256: the row tiles per workgroup are chosen for the least rounds x (tiles + 2) (the 2:
-        // what a workgroup costs besides its MFMAs, in tiles).
-        const int swn = NT >= 600 ? 4 : 2, swk = 8 / swn;
-        const int groups = ((NT + 4 * swn - 1) / (4 * swn) + 7) / 8 * 8;
-        int best_tm = 0, best_cost = 1 << 30;
-        for (int t : {8, 6, 5, 4, 3}) {
-            const int shares = (m_tiles + t - 1) / t, tm = (m_tiles + shares - 1) / shares;   // tm <= t
-            if (tm < 3 || !wide_params(tm, 4, swn, swk).valid) continue;
-            const int cost = ((groups * shares + 255) / 256) * (tm + 2);
-            if (cost < best_cost) { best_cost = cost; best_tm = tm; }
+        // an activation fragment read from LDS four), 4 x 2 wavefronts (sixteen n-tiles per workgroup) or 2 x 4
+        // (eight, K split four ways inside the workgroup).  One such workgroup fills a CU, so the launch runs in whole
+        // rounds of 256: shape and row tiles per workgroup are chosen for the least rounds x (tiles + 2) x k-tiles per
+        // wavefront (the 2: what a workgroup costs besides its MFMAs, in tiles); 2 x 4, whose activation fragments feed
+        // half as many wavefronts, costs about 1.2 times as much per MFMA (4096 x 4096 at 1999 rows: 191 us as 672
+        // workgroups in three rounds, 126 us as 256 in one; at 768 rows 2 x 4 fills the chip, 4 x 2 three eighths).
+        int best_tm = 0, best_wn = 4, best_cost = 1 << 30;
+        for (int swn : {4, 2}) {
+            const int groups = ((NT + 4 * swn - 1) / (4 * swn) + 7) / 8 * 8;
+            for (int t : {8, 6, 5, 4, 3}) {
+                const int shares = (m_tiles + t - 1) / t, tm = (m_tiles + shares - 1) / shares;   // tm <= t
+                if (tm < 3 || !wide_params(tm, 4, swn, 8 / swn).valid) continue;
+                const int cost = ((groups * shares + 255) / 256) * (tm + 2) * (swn == 4 ? 20 : 12);
+                if (cost < best_cost) { best_cost = cost; best_tm = tm; best_wn = swn; }
+            }
         }
         if (best_tm > 0) {
-            p.wide = true; p.wn = swn; p.wk = swk; p.tm = best_tm; p.tn = 4; p.sk = 1; p.ms = (m_tiles + best_tm - 1) / best_tm;
+            p.wide = true; p.wn = best_wn; p.wk = 8 / best_wn; p.tm = best_tm; p.tn = 4; p.sk = 1; p.ms = (m_tiles + best_tm - 1) / best_tm;
             return p;
         }
     }
