@@ -139,15 +139,10 @@ __global__ void rope_table_kernel(float *table, int n_pos, int half, int dh, flo
     table[2 * idx + 1] = (float)sn;
 }
 
-// Rotate q and k of the new rows (pair (i, i + dh/2)), store q for the attention kernel and append k, v to
-// the KV cache.  One workgroup per (row, head).
-//   bf16: K cache [H][cap][dh], V cache chunk-tiled transposed [H][cap/32][dh][32] (vt_offset: the attention
-//         kernel reads V^T fragments);
-//         q as hi/lo bf16 planes; an fp32 copy of the new k, v feeds the in-flight attention segment
-//   fp32: K and V caches [H][cap][dh], q fp32
-template <bool BF16>
+// Rotate q and k of the new rows (pair (i, i + dh/2)), store q for the attention kernel and append k, v to the cache.
+// fp32 path: one workgroup per (row, head); K and V caches [H][cap][dh].
 __global__ __launch_bounds__(64) void rope_kv_kernel(const float *__restrict__ qkv, const float *__restrict__ table,
-                                                     void *q_out, size_t q_plane, void *k_shared, void *v_shared,
+                                                     float *q_out, void *k_shared, void *v_shared,
                                                      void *k_priv, void *v_priv,
                                                      const int32_t *private_len, int M, int T, int H, int dh, int S,
                                                      int prefill_shared, int cap_shared, int cap_priv,
@@ -155,15 +150,7 @@ __global__ __launch_bounds__(64) void rope_kv_kernel(const float *__restrict__ q
     const int r = blockIdx.x, h = blockIdx.y;
     const int HD = H * dh, half = dh >> 1;
     if (r >= M) {   // padding rows of the q tile: zeros
-        for (int c = threadIdx.x; c < dh; c += 64) {
-            const size_t o = (size_t)r * HD + h * dh + c;
-            if (BF16) {
-                reinterpret_cast<uint16_t *>(q_out)[o] = 0;
-                reinterpret_cast<uint16_t *>(q_out)[o + q_plane] = 0;
-            } else {
-                reinterpret_cast<float *>(q_out)[o] = 0.f;
-            }
-        }
+        for (int c = threadIdx.x; c < dh; c += 64) q_out[(size_t)r * HD + h * dh + c] = 0.f;
         return;
     }
     const int b = r / T, j = r - b * T;
@@ -191,34 +178,85 @@ __global__ __launch_bounds__(64) void rope_kv_kernel(const float *__restrict__ q
         const float k1 = row[HD + i], k2 = row[HD + i + half];
         const float v1 = row[2 * HD + i], v2 = row[2 * HD + i + half];
         const float c = tb[2 * i], s_ = tb[2 * i + 1];
-        const float qa = q1 * c - q2 * s_, qb = q2 * c + q1 * s_;
-        const float ka = k1 * c - k2 * s_, kb = k2 * c + k1 * s_;
         const size_t qo = (size_t)r * HD + h * dh + i;
-        if (BF16) {
-            uint16_t *q16 = reinterpret_cast<uint16_t *>(q_out);
-            split_bf16(qa, q16[qo], q16[qo + q_plane]);              // q = hi + lo planes
-            split_bf16(qb, q16[qo + half], q16[qo + half + q_plane]);
-            if (store_kv) {
-                uint16_t *kc = reinterpret_cast<uint16_t *>(prefill_shared ? k_shared : k_priv);
-                uint16_t *vc = reinterpret_cast<uint16_t *>(prefill_shared ? v_shared : v_priv);
-                const size_t head = prefill_shared ? (size_t)h : ((size_t)b * H + h);
-                kc[(head * cap + idx) * dh + i] = f2bf(ka);
-                kc[(head * cap + idx) * dh + i + half] = f2bf(kb);
-                vc[head * dh * cap + vt_offset(i, idx, dh)] = f2bf(v1);
-                vc[head * dh * cap + vt_offset(i + half, idx, dh)] = f2bf(v2);
-            }
+        q_out[qo] = q1 * c - q2 * s_;
+        q_out[qo + half] = q2 * c + q1 * s_;
+        if (store_kv) {
+            float *kc = reinterpret_cast<float *>(prefill_shared ? k_shared : k_priv);
+            float *vc = reinterpret_cast<float *>(prefill_shared ? v_shared : v_priv);
+            const size_t head = prefill_shared ? (size_t)h : ((size_t)b * H + h);
+            kc[(head * cap + idx) * dh + i] = k1 * c - k2 * s_;
+            kc[(head * cap + idx) * dh + i + half] = k2 * c + k1 * s_;
+            vc[(head * cap + idx) * dh + i] = v1;
+            vc[(head * cap + idx) * dh + i + half] = v2;
+        }
+    }
+}
+
+// bf16 path, shared-prefix prefill (verify and decode steps rotate inside the attention launch): q as hi/lo bf16 planes,
+// K cache [H][cap][dh], V cache chunk-tiled transposed [H][cap/32][dh][32] (vt_offset).
+// One workgroup per (32-key chunk of the cache, head), so that the transposed values leave as whole 16-byte pieces
+// through LDS: a workgroup per (row, head) scattered them in 2-byte stores 64 bytes apart (64 us for 1999 rows of 32
+// heads, now 32 us).  Chunks at the ends of the prompt are partly old or future keys: only the rows at hand are
+// written there.
+template <int DH>
+__global__ __launch_bounds__(256) void rope_kv_prefill_kernel(const float *__restrict__ qkv, const float *__restrict__ table,
+                                                              uint16_t *q_out, size_t q_plane, uint16_t *k_cache, uint16_t *v_cache,
+                                                              int M, int Mq, int H, int S, int cap) {
+    constexpr int HALF = DH / 2, QUADS = HALF / 4, LD = 40;   // (rows of 80 bytes: 16-byte aligned, spread over banks)
+    __shared__ __attribute__((aligned(16))) uint16_t vt[DH][LD];
+    const int h = blockIdx.y, key0 = (S / 32 + blockIdx.x) * 32, HD = H * DH;
+    for (int it = threadIdx.x; it < 32 * QUADS; it += 256) {
+        const int rr = it / QUADS, i = (it - rr * QUADS) * 4;
+        const int key = key0 + rr, j = key - S;
+        if (j < 0 || j >= M) continue;
+        const float *row = qkv + (size_t)j * 3 * HD + h * DH + i;
+        auto ld4 = [](const float *p) { return *reinterpret_cast<const f32x4 *>(p); };
+        const f32x4 q1 = ld4(row), q2 = ld4(row + HALF), k1 = ld4(row + HD), k2 = ld4(row + HD + HALF);
+        const f32x4 v1 = ld4(row + 2 * HD), v2 = ld4(row + 2 * HD + HALF);
+        const float *tb = table + (size_t)key * DH + 2 * i;
+        const f32x4 t0 = ld4(tb), t1 = ld4(tb + 4);
+        const float c[4] = {t0[0], t0[2], t1[0], t1[2]}, sn[4] = {t0[1], t0[3], t1[1], t1[3]};
+        uint16_t qh[2][4], ql[2][4], kb[2][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            split_bf16(q1[e] * c[e] - q2[e] * sn[e], qh[0][e], ql[0][e]);
+            split_bf16(q2[e] * c[e] + q1[e] * sn[e], qh[1][e], ql[1][e]);
+            kb[0][e] = f2bf(k1[e] * c[e] - k2[e] * sn[e]);
+            kb[1][e] = f2bf(k2[e] * c[e] + k1[e] * sn[e]);
+            vt[i + e][rr] = f2bf(v1[e]);
+            vt[i + e + HALF][rr] = f2bf(v2[e]);
+        }
+        auto st4 = [](uint16_t *p, const uint16_t *v) {
+            const uint2 w = {(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16)};
+            *reinterpret_cast<uint2 *>(p) = w;
+        };
+        uint16_t *qp = q_out + (size_t)j * HD + h * DH + i;
+        uint16_t *kp = k_cache + ((size_t)h * cap + key) * DH + i;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            st4(qp + z * HALF, qh[z]);
+            st4(qp + z * HALF + q_plane, ql[z]);
+            st4(kp + z * HALF, kb[z]);
+        }
+    }
+    if (blockIdx.x == gridDim.x - 1)                          // padding rows of the q tile: zeros
+        for (int it = threadIdx.x; it < (Mq - M) * DH; it += 256) {
+            const size_t o = (size_t)(M + it / DH) * HD + h * DH + it % DH;
+            q_out[o] = 0;
+            q_out[o + q_plane] = 0;
+        }
+    __syncthreads();
+    uint16_t *vc = v_cache + (size_t)h * DH * cap + vt_offset(0, key0, DH);
+    const bool whole = key0 >= S && key0 + 32 <= S + M;       // (uniform)
+    for (int it = threadIdx.x; it < DH * 4; it += 256) {
+        const int d = it >> 2, k8 = (it & 3) * 8;
+        if (whole) {
+            *reinterpret_cast<u32x4 *>(vc + d * 32 + k8) = *reinterpret_cast<const u32x4 *>(&vt[d][k8]);
         } else {
-            float *q32 = reinterpret_cast<float *>(q_out);
-            q32[qo] = qa;
-            q32[qo + half] = qb;
-            if (store_kv) {
-                float *kc = reinterpret_cast<float *>(prefill_shared ? k_shared : k_priv);
-                float *vc = reinterpret_cast<float *>(prefill_shared ? v_shared : v_priv);
-                const size_t head = prefill_shared ? (size_t)h : ((size_t)b * H + h);
-                kc[(head * cap + idx) * dh + i] = ka;
-                kc[(head * cap + idx) * dh + i + half] = kb;
-                vc[(head * cap + idx) * dh + i] = v1;
-                vc[(head * cap + idx) * dh + i + half] = v2;
+            for (int e = 0; e < 8; ++e) {
+                const int j = key0 + k8 + e - S;
+                if (j >= 0 && j < M) vc[d * 32 + k8 + e] = vt[d][k8 + e];
             }
         }
     }
@@ -419,14 +457,20 @@ int launch_rope_kv(bool bf16, const float *qkv, const float *rope_table, void *q
                    void *k_shared, void *v_shared, void *k_priv, void *v_priv,
                    const int32_t *private_len, int M, int Mq, int T, int H, int dh, int S, int prefill_shared,
                    int cap_shared, int cap_priv, int max_private, int32_t *status, hipStream_t st) {
-    if (bf16)
-        hipLaunchKernelGGL(rope_kv_kernel<true>, dim3(Mq, H), dim3(64), 0, st, qkv, rope_table, q_out, q_plane,
+    if (bf16) {
+        if (!prefill_shared || (dh != 64 && dh != 128)) { set_error("rope_kv: the bf16 form is the shared-prefix prefill's"); return SEED_E_INVALID_ARG; }
+        const dim3 grid((S + M + 31) / 32 - S / 32, H);
+        if (dh == 128)
+            hipLaunchKernelGGL(rope_kv_prefill_kernel<128>, grid, dim3(256), 0, st, qkv, rope_table, (uint16_t *)q_out, q_plane,
+                               (uint16_t *)k_shared, (uint16_t *)v_shared, M, Mq, H, S, cap_shared);
+        else
+            hipLaunchKernelGGL(rope_kv_prefill_kernel<64>, grid, dim3(256), 0, st, qkv, rope_table, (uint16_t *)q_out, q_plane,
+                               (uint16_t *)k_shared, (uint16_t *)v_shared, M, Mq, H, S, cap_shared);
+    } else {
+        hipLaunchKernelGGL(rope_kv_kernel, dim3(Mq, H), dim3(64), 0, st, qkv, rope_table, (float *)q_out,
                            k_shared, v_shared, k_priv, v_priv, private_len, M, T, H, dh, S,
                            prefill_shared, cap_shared, cap_priv, max_private, status);
-    else
-        hipLaunchKernelGGL(rope_kv_kernel<false>, dim3(Mq, H), dim3(64), 0, st, qkv, rope_table, q_out, q_plane,
-                           k_shared, v_shared, k_priv, v_priv, private_len, M, T, H, dh, S,
-                           prefill_shared, cap_shared, cap_priv, max_private, status);
+    }
     return hip_fail(hipGetLastError(), "rope_kv launch");
 }
 
