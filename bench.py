@@ -314,7 +314,7 @@ def measure_verify(w, args, dev, with_inputs=False):
                  "mfma_frac": flops / (ms_per_step * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
                  "mfma_frac_ceiling_at_hbm_peak": min(1.0, N * G / (MFMA_BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9))),
                  "accepted_tokens": accepted, "wall_ms_per_step": wall_ms},
-        "roofline": {"bound": "hbm", "kernel": "gemm_kernel / gemm_wide_kernel (weight-streaming projection)",
+        "roofline": {"bound": "hbm", "kernel": "gemm_stream_kernel / gemm_wide_kernel (weight-streaming projection)",
                      "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_gbs / HBM_PEAK_GBS,
                      "traffic": traffic[0], "traffic_source": traffic[1],
                      "launches_per_step": launches / args.steps, "bytes_per_launch": bytes_per_launch,

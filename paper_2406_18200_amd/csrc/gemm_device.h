@@ -14,10 +14,10 @@ __device__ __forceinline__ void pin_args(const GemmArgs &a) {
 
 // 8-bit weights (context dtype SEED_DTYPE_BF16_W8): the same tiles with one byte per weight, an OCP e4m3 code
 // (sign, 4 exponent bits of bias 7, 3 mantissa bits; no infinities), and one float scale per output feature:
-// tile (nt, kt) is 512 bytes, lane l holding the 8 codes of W[nt*16 + l%16][kt*32 + 8*(l/16) .. +8].  Half the
-// bytes cross HBM; on the way into the MFMA every code is widened to the bf16 of the same value (exact: three
-// mantissa bits) with the hardware's packed fp8 -> float32 conversion, and the scale multiplies the fp32 sums once,
-// after the k loop (before anything is exchanged or reduced: scaling is linear).
+// two consecutive k-tiles of an n-tile are 1 KiB, lane l holding the 8 codes of W[nt*16 + l%16][kt*32 + 8*(l/16) .. +8]
+// of the first, then of the second.  Half the bytes cross HBM; on the way into the MFMA every code is widened to the bf16 of the same value (exact: three
+// mantissa bits) with the hardware's packed fp8 -> float32 conversion, and the scale multiplies the finished fp32 sums
+// once, in the epilogue.
 __device__ __forceinline__ bf16x8 widen_e4m3(u32x2 c) {
     u32x4 r;
 #pragma unroll
@@ -33,8 +33,9 @@ __device__ __forceinline__ bf16x8 widen_e4m3(u32x2 c) {
 // 4-bit weights (context dtype SEED_DTYPE_BF16_W4): the OCP microscaling format MXFP4 -- elements are E2M1 codes
 // (sign, two exponent bits, one mantissa bit: 0, 0.5, 1, 1.5, 2, 3, 4, 6), every 32 consecutive inputs of an output
 // feature share a power-of-two scale stored as an E8M0 byte (2^(e - 127)).  A k-tile is exactly one such block per
-// row: tile (nt, kt) is 256 bytes of codes, lane l holding the 8 codes of W[nt*16 + l%16][kt*32 + 8*(l/16) .. +8]
-// (input k in the low nibble of byte k/2 for even k), plus 16 scale bytes in a separate array [nt][kt][16].
+// row: two consecutive k-tiles of an n-tile are 512 bytes of codes, lane l holding the 8 codes of
+// W[nt*16 + l%16][kt*32 + 8*(l/16) .. +8] of the first, then of the second (input k in the low nibble of byte k/2 for
+// even k), plus 32 scale bytes in a separate array [nt][pair][16 rows][2].
 // On the way into the MFMA a code pair becomes a bf16 pair with the hardware's scaled conversion (exact: one
 // mantissa bit times a power of two), so the kernel computes with exactly the values the codes stand for.
 __device__ __forceinline__ bf16x8 widen_mxfp4(uint32_t c, uint32_t e8m0) {
@@ -53,9 +54,8 @@ __device__ __forceinline__ bf16x8 widen_mxfp4(uint32_t c, uint32_t e8m0) {
 }
 
 // Which column group and which share of the rows this workgroup works on.  With MS > 1 the rows of a step are
-// split over MS workgroups per column group (TM row tiles each): every workgroup then stages and re-reads only
-// its own rows' activations through LDS -- the saturated resource at 65..128 rows -- and takes MS times the columns
-// instead.  The MS workgroups of a column group read the same weights; they are laid out so that they run on the
+// split over MS workgroups per column group (TM row tiles each): every workgroup then reads only its own rows'
+// activations and takes MS times the columns instead.  The MS workgroups of a column group read the same weights; they are laid out so that they run on the
 // SAME XCD at the same time (workgroups go to the eight XCDs round robin in launch order, so ids L and L + 8 are
 // neighbours in time on one XCD): the second request finds the line in that XCD's L2 and HBM is still read once.
 // The grid is rounded up to whole rounds of eight column groups; padding workgroups return at once.
