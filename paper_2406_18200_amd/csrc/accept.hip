@@ -230,82 +230,6 @@ __device__ int draw_fixed(const TargetRow &row, const float *q, float u, int V, 
     return sm.tok;
 }
 
-// The same draw in one pass over memory: lane l of wavefront w holds the weights of the 32 consecutive tokens from
-// 2048 w + 32 l on in registers (eight 16-byte loads per array, all in flight at once), so the wavefront whose
-// segment holds the target walks them without a second, uncoalesced pass.  The draw is a chain of memory round
-// trips on one CU, and this leaves one of them: accept_resample_kernel of 16 branches x 6 rows of 32000 logits 22.5
-// -> 19 us.  For rows of up to 32768 tokens whose length and addresses are multiples of four floats; same token (the
-// sums are integers).
-constexpr int kOncePerLane = 32;
-__device__ __forceinline__ bool draw_once_fits(const TargetRow &row, const float *q, int V) {
-    return V <= kBlock * kOncePerLane && V >= 4 && (V & 3) == 0 && (((uintptr_t)row.src | (uintptr_t)q) & 15) == 0;
-}
-template <int RESIDUAL>
-__device__ int draw_fixed_once(const TargetRow &row, const float *q, float u, int V, Shared &sm) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int v0 = (int)threadIdx.x * kOncePerLane;
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    f32x4_t x[kOncePerLane / 4], y[kOncePerLane / 4];
-#pragma unroll
-    for (int i = 0; i < kOncePerLane / 4; ++i) {              // (past the end: the last quad again, masked below)
-        const int v = min(v0 + 4 * i, V - 4);
-        x[i] = *reinterpret_cast<const f32x4_t *>(row.src + v);
-        if (RESIDUAL) y[i] = *reinterpret_cast<const f32x4_t *>(q + v);
-    }
-    unsigned long long mine = 0;
-#pragma unroll
-    for (int e = 0; e < kOncePerLane; ++e) {
-        const float p = row.is_logits ? exp_scaled(x[e >> 2][e & 3], row.mx, row.inv_temp) * row.inv_sum : x[e >> 2][e & 3];
-        float w = p;
-        if (RESIDUAL) {
-            w = __fsub_rn(p, y[e >> 2][e & 3]);
-            w = w > 0.f ? w : 0.f;
-        }
-        w = v0 + e < V ? w : 0.f;
-        x[e >> 2][e & 3] = w;
-        mine += to_fixed(w);
-    }
-    unsigned long long incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long o = __shfl_up(incl, off);
-        if (lane >= off) incl += o;
-    }
-    __syncthreads();
-    if (lane == 63) sm.tot[wave] = incl;
-    if (threadIdx.x == 0) sm.tok = -1;
-    __syncthreads();
-    unsigned long long Z = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) Z += sm.tot[i];
-    if (Z == 0) return -1;
-    const unsigned long long m24 = (unsigned long long)(__fmul_rn(u, 16777216.0f));
-    const unsigned long long t = (m24 * Z) >> 24;
-    unsigned long long run = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i)
-        if (i < wave) run += sm.tot[i];
-    const unsigned long long before = run + incl - mine;      // weights of all tokens ahead of this lane's
-    if (before <= t && before + mine > t) {                   // (exactly one lane: t < Z)
-        unsigned long long c = before;
-        int tok = -1;
-#pragma unroll
-        for (int e = 0; e < kOncePerLane; ++e) {
-            c += to_fixed(x[e >> 2][e & 3]);
-            if (tok < 0 && c > t) tok = v0 + e;
-        }
-        sm.tok = tok;
-    }
-    __syncthreads();
-    return sm.tok;
-}
-
-// (uniform over the workgroup: the choice depends on the row's length and addresses only)
-template <int RESIDUAL>
-__device__ int draw_row(const TargetRow &row, const float *q, float u, int V, Shared &sm) {
-    return draw_once_fits(row, q, V) ? draw_fixed_once<RESIDUAL>(row, q, u, V, sm) : draw_fixed<RESIDUAL>(row, q, u, V, sm);
-}
-
 // Statistics of one slice of a row of logits, written by row_stats_kernel: the maximum, its lowest index, and
 // the sum of exp((x - that maximum) / temperature) over the slice.
 struct SliceStats {
@@ -533,10 +457,10 @@ __global__ __launch_bounds__(kBlock) void accept_resample_kernel(seed_accept_arg
                 const TargetRow row{rsrc, is_logits, ri.mx[r2], ri.sum[r2], 1.0f / a.temperature};
                 if (rej_row >= 0) {
                     const float *q = a.q + ((size_t)b * G + j) * V;
-                    new_tok = draw_row<1>(row, q, a.u_res[b], V, sm);
-                    if (new_tok < 0) new_tok = draw_row<0>(row, nullptr, a.u_res[b], V, sm);
+                    new_tok = draw_fixed<1>(row, q, a.u_res[b], V, sm);
+                    if (new_tok < 0) new_tok = draw_fixed<0>(row, nullptr, a.u_res[b], V, sm);
                 } else {
-                    new_tok = draw_row<0>(row, nullptr, a.u_res[b], V, sm);
+                    new_tok = draw_fixed<0>(row, nullptr, a.u_res[b], V, sm);
                 }
             }
             rej_row = -1;
@@ -992,7 +916,7 @@ __global__ __launch_bounds__(kBlock) void accept_tree_kernel(seed_accept_args a,
                 new_tok = ts.best[cur];
             } else {
                 new_tok = dead ? -1 : draw_tree_residual(row, q, n_rej, ts.Z, a.u_res[b], V, sm);
-                if (new_tok < 0) new_tok = draw_row<0>(row, nullptr, a.u_res[b], V, sm);
+                if (new_tok < 0) new_tok = draw_fixed<0>(row, nullptr, a.u_res[b], V, sm);
             }
             break;
         }
@@ -1008,7 +932,7 @@ __global__ __launch_bounds__(kBlock) void accept_tree_kernel(seed_accept_args a,
     }
     if (acc == G && Tp == n_nodes && n_par < n_nodes) {                 // bonus rows: a token after a full path
         if (a.greedy) new_tok = ts.best[cur];
-        else new_tok = draw_row<0>(row_of(cur), nullptr, a.u_res[b], V, sm);
+        else new_tok = draw_fixed<0>(row_of(cur), nullptr, a.u_res[b], V, sm);
     }
     for (int j = acc + threadIdx.x; j <= G; j += kBlock) a.out_tok[(size_t)b * (G + 1) + j] = (j == acc) ? new_tok : -1;
     if (a.path_node != nullptr)
@@ -1034,7 +958,7 @@ __global__ __launch_bounds__(kBlock) void sample_probs_kernel(const float *probs
     __shared__ Shared sm;
     const int b = blockIdx.x;
     TargetRow row{probs + (size_t)b * row_stride, 0, 0.f, 1.f, 1.f};
-    int tok = draw_row<0>(row, nullptr, u[b], V, sm);
+    int tok = draw_fixed<0>(row, nullptr, u[b], V, sm);
     if (threadIdx.x == 0) tok_out[b] = tok;
 }
 
