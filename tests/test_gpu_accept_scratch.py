@@ -1,5 +1,5 @@
-"""The accept / resample step with caller-provided scratch, and the one-pass draw at the edges of its range (whole quads,
-32768 tokens, misaligned rows), against the oracle and the entry point without scratch."""
+"""The accept / resample step with caller-provided scratch against the entry point without, and the draw at vocabulary
+sizes around its segment boundaries and from misaligned rows against the oracle."""
 import ctypes as C
 
 import numpy as np
@@ -22,8 +22,8 @@ def _inputs(N, G, V):
 
 
 @pytest.mark.parametrize("V", [4, 36, 2044, 2046, 2048, 32764, 32768, 32772])
-def test_one_pass_draw_is_bit_exact(V):
-    """PROBS mode with bonus rows: residual and plain draws; V = 2046 and 32772 take the two-pass form."""
+def test_draw_at_segment_edges_is_bit_exact(V):
+    """PROBS mode with bonus rows: residual and plain draws."""
     import paper_2406_18200_amd as sv
     z, q, drafts, u_acc, u_res = _inputs(5, 3, V)
     p = oracle.softmax_temperature(z, 1.0)
